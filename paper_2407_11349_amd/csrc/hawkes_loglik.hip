@@ -2017,17 +2017,17 @@ __device__ inline void plan_ranges(const PlanArgs &a)
 }
 
 // First tile the block of rows [i0, i1) that starts at t0 visits: from there on triggering terms
-// matter to its rows or background terms to its rows or the tile's (with bounds), and all
-// is within the triggering range.
+// matter to its rows, background terms to its rows (its own gap) or to the tile's (their reach, in the
+// symmetric sweep), and all is within the triggering range.  Each condition is monotone in the tile.
 __device__ inline int first_tile_needed(const PlanArgs &a, int64_t i0, int64_t i1, double t0, double gap, double range)
 {
     const double limit = double(rows_bound(a.bounds, i0, i1).trig) - RATE_BITS +
                          double(float(a.omega * LOG2E)) * (t0 - a.tile[1]);
-    const double from = a.sym ? t0 : t0 - gap;
     int lo = 0, hi = a.num_tiles;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
-        if (a.tile[3 * mid + 1] < t0 - range || (a.far_trig[mid] < limit && a.reach[mid] < from))
+        const double last = a.tile[3 * mid + 1];
+        if (last < t0 - range || (last < t0 - gap && a.reach[mid] < t0 && a.far_trig[mid] < limit))
             lo = mid + 1;
         else
             hi = mid;
