@@ -2108,9 +2108,12 @@ __device__ __forceinline__ void plan(const PlanArgs &a, double umax, int flags)
     }
     if (!a.sym)
         return;
-    // a group's first tile: the least of its blocks' and, so that gclo is nondecreasing, of the later groups'
+    // a group's first tile: the least of its blocks' and, so that gclo is nondecreasing, of the later groups'.
+    // Where the data checks failed it is 0: with unsorted times gchi need not be nondecreasing, and
+    // k_fold's cells of a column then fall with the row group only if gclo is 0 throughout
+    const bool cull = a.trig_cull && !flags;
     int first = a.num_tiles;
-    if (a.trig_cull) {
+    if (cull) {
         __syncthreads();  // the blocks' words
         if (tid < a.num_gr)
             for (int64_t b = int64_t(tid) * a.rr; b < a.num_tb && b < int64_t(tid + 1) * a.rr; ++b) {
@@ -2134,7 +2137,7 @@ __device__ __forceinline__ void plan(const PlanArgs &a, double umax, int flags)
         const int64_t bl = (bf + a.rr < a.num_tb ? bf + a.rr : a.num_tb) - 1;
         const int hi = int((int64_t(tile_end(bl)) * TS + a.cg - 1) / a.cg) - 1;
         int lo = 0;
-        if (a.trig_cull) {
+        if (cull) {
             lo = int(int64_t(first) * TS / a.cg);
             lo = lo < hi ? lo : hi;
         }
