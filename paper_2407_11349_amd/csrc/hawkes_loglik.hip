@@ -2004,7 +2004,8 @@ __device__ inline void plan_ranges(const PlanArgs &a)
         pt = at;
         pr = ar;
     } else {
-        pv += av * decay(pt - at);
+        if (wave > 0)  // the first wave has none before it, and pt may lie far before t_chunk
+            pv += av * decay(pt - at);
         pr = fmax(pr, ar);
     }
     const double t_first = a.tile[1];

@@ -128,3 +128,28 @@ def test_the_bound_holds_on_other_sets(form, omega):
     back, trig = _left_out(t, x, y, s, th, exact, plan, rows)
     print(f"{form} omega={omega}: left out: background {back:.2e}, triggering {trig:.2e} of the rate", flush=True)
     assert back <= 2.0 ** -60 and trig <= 2.0 ** -60
+
+
+@pytest.mark.parametrize("omega", [2.0, 5.0, 20.0])
+@pytest.mark.parametrize("n, days", [(16600, 1200.0), (20000, 3000.0)])
+def test_ranges_are_as_short_as_the_terms_allow(n, days, omega):
+    """Where triggering is over long before the background's gaps (by hundreds of bits), no block visits a tile
+    beyond its own and the tiles' gaps: also where a step from one tile to the next is more than an FP32
+    exponential spans."""
+    rng = np.random.default_rng(n)  # all at one place: every row has near neighbours, so that its gap is narrow
+    t = np.sort(rng.uniform(0.0, days, n))
+    x, y = rng.normal(size=(2, n))
+    th = synth.theta_default()
+    th[5] = omega
+    dev = hk.DeviceEvents.from_arrays(t, x, y, np.ones(n))
+    ws = hk.Workspace(n, "fp32_skip")
+    hk.loglik_grad(dev, th, precision="fp32_skip", ws=ws)
+    plan = _plan(ws, n)
+    blocks = plan[::2]
+    for b in range(len(blocks)):
+        # beyond the block's gap, and every tile so far beyond its own
+        reach = np.maximum.accumulate(plan["last"] + np.repeat(blocks["gap"], 2)[:len(plan)])
+        beyond = (plan["last"] < blocks["first"][b] - float(blocks["gap"][b])) & (reach < blocks["first"][b])
+        assert blocks["klo"][b] >= beyond.sum(), (b, beyond.sum())
+    assert blocks["gap"][1:].max() < 0.9 * blocks["gap"][0]  # the first rows have no event before them
+    print(f"gaps {blocks['gap'][0]:.1f}, then up to {blocks['gap'][1:].max():.1f}", flush=True)
