@@ -47,6 +47,7 @@
 
 #include "hawkes.h"
 #include "hawkes_common.h"
+#include "hawkes_gelu.h"
 #include "hawkes_mlp.h"
 
 namespace hawkes {
@@ -160,45 +161,6 @@ __device__ inline uint16_t f32_to_bf16(float f)
         return uint16_t((u >> 16) | 0x40u);
     const uint32_t lsb = (u >> 16) & 1u;
     return uint16_t((u + 0x7fffu + lsb) >> 16);
-}
-
-constexpr float K_SQRT1_2 = 0.70710678118654752440f;
-constexpr float K_INV_SQRT_2PI = 0.39894228040143267794f;
-
-__device__ inline float gelu(float x) { return 0.5f * x * (1.0f + erff(x * K_SQRT1_2)); }
-__device__ inline float gelu_d1(float x)
-{
-    return 0.5f * (1.0f + erff(x * K_SQRT1_2)) + x * K_INV_SQRT_2PI * expf(-0.5f * x * x);
-}
-__device__ inline float gelu_d2(float x) { return K_INV_SQRT_2PI * expf(-0.5f * x * x) * (2.0f - x * x); }
-
-// GELU and its slope Phi + x phi from one exponential, for batched inference (training
-// keeps erff and expf): Phi(-u) = e^(-u^2/2) t Q(t) with t = 1/(1 + 0.27 u), u = |x|, and Q
-// the degree-8 polynomial that fits R(u)/t, R = Phi(-u) e^(u^2/2) (half the scaled
-// complementary error function at u/sqrt 2), over 0 <= u <= 13.5 with the least largest
-// relative error, 2.3e-8 (Lawson's iteration; past 13.5 the exponential is below
-// 1e-39).  In FP32: GELU within 3.9e-7 and the slope within 1.9e-7 of their values over
-// [-14, 14], rms 4.6e-8 and 2.1e-8; with erff and expf 4.5e-7, 1.4e-7, 5.1e-8 and 1.9e-8.
-// About 22 instructions instead of 75, which were the kernel's largest part by far.
-struct Gelu {
-    float a, d1;
-};
-__device__ __forceinline__ Gelu gelu_all(float x)
-{
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.27f, fabsf(x), 1.0f));
-    const float e = __builtin_amdgcn_exp2f(x * x * -0.72134752044448170368f);
-    float q = 2.885542323e-02f;
-    q = fmaf(q, t, -1.259534110e-01f);
-    q = fmaf(q, t, 1.686420532e-01f);
-    q = fmaf(q, t, -6.784449505e-02f);
-    q = fmaf(q, t, 1.068362740e-01f);
-    q = fmaf(q, t, 7.249333263e-02f);
-    q = fmaf(q, t, 1.016905477e-01f);
-    q = fmaf(q, t, 1.075607488e-01f);
-    q = fmaf(q, t, 1.077195380e-01f);
-    q = q * t * e;
-    const float phi = (x >= 0.0f) ? 1.0f - q : q;
-    return Gelu{x * phi, fmaf(x * K_INV_SQRT_2PI, e, phi)};
 }
 
 // One-sample evaluation: value and input gradient by a workgroup of two groups
