@@ -153,8 +153,10 @@ size_t hawkes_workspace_bytes(int64_t n, int precision);
 
 /* The smallest workspace the calls accept for n events at `precision` with
  * default options (0 if the arguments are invalid): the part linear in n and
- * the slot of one workgroup, so that the sweep runs one workgroup per pass.
- * Between this and hawkes_workspace_bytes() the results are the same and
+ * the slot of one workgroup.  The passes before the last then run the
+ * workgroups whose slots the space of the row values holds too (60 bytes per
+ * event): a call takes about 10 times as long as in hawkes_workspace_bytes()
+ * at 2,000 to 20,000 events.  Between this and hawkes_workspace_bytes() the results are the same and
  * only the number of passes changes.  Options that enlarge a workgroup's
  * slot (fewer symmetric groups) may need more: such calls return
  * HAWKES_EWORKSPACE.  The minimum does not decrease with n, so a workspace

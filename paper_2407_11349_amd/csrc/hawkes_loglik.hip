@@ -2978,6 +2978,12 @@ T *at(void *ws, size_t off)
 
 enum Mode { MODE_LOGLIK, MODE_GRAD, MODE_TERMS };
 
+// The slots of a pass: `cap` cells' row sums, then their column sums.
+struct Slots {
+    double *row = nullptr, *col = nullptr;
+    int64_t cap = 0;
+};
+
 // The work plan of a call (cells and their slots) and its workspace arrays.
 struct Setup {
     Plan P;
@@ -2989,9 +2995,12 @@ struct Setup {
     CellMap cells;
     int rr = 1, cg = TB, ge = TB;  // target blocks and sources per group; rows per row group
     int row_planes = 6, col_planes = 3;  // sums the call's sweep writes
+    double *slots = nullptr;         // the slot region
     size_t slot_avail = 0;
-    int64_t cells_ub = 0, cap = 0, passes = 0;
-    double *srow = nullptr, *scol = nullptr;
+    double *early_slots = nullptr;   // the same with the row values' and the rescue list's space before it
+    size_t early_avail = 0;
+    int64_t cells_ub = 0, passes = 0, last_cell0 = 0;
+    Slots early, last;               // of the last pass and of those before it
 };
 
 int setup(const hawkes_events *ev, int64_t rb, int64_t re, void *ws, size_t ws_bytes, const Layout &L,
@@ -3036,7 +3045,9 @@ int setup(const hawkes_events *ev, int64_t rb, int64_t re, void *ws, size_t ws_b
     S.cells_ub = int64_t(S.cells.num_gr) * S.cells.num_gc;
     S.acc_row = at<double>(ws, L.acc);
     S.acc_col = S.acc_row + 6 * S.P.rows_pad;
-    S.srow = at<double>(ws, L.slots);
+    S.slots = at<double>(ws, L.slots);
+    S.early_slots = at<double>(ws, L.rowvals);
+    S.early_avail = ws_bytes - L.rowvals;
     return HAWKES_OK;
 }
 
@@ -3250,21 +3261,41 @@ int device_concurrency(const void *kernel)
 // whole rounds of the workgroups the device runs at once (so that a pass ends
 // without a ragged round of its own).  A slot holds only the sums the call's sweep
 // writes (a third of all without the gradient).
+//   Where that does not fill the device, the passes before the last also use the
+// space of the row values and the rescue list (60 bytes per row), which the last
+// pass's fold is the first to write.  At the minimum workspace the region holds one or two
+// cells of the default plan, narrower than the square cell it is sized for; with those alone in a pass a
+// gradient took 2.47, 19.8 and 96.3 ms at 2,000, 9,000 and 20,000 events (FP32), so it takes 0.51,
+// 1.02 and 2.27 (0.05, 0.10 and 0.23 in the default workspace).
 void plan_passes(Setup &S, const void *kernel, int row_planes, int col_planes)
 {
     S.row_planes = row_planes;
     S.col_planes = S.sym ? col_planes : 0;
-    int64_t cap = int64_t(S.slot_avail / (sizeof(double) * (size_t(row_planes) * S.ge + size_t(S.col_planes) * S.cg)));
-    if (cap >= S.cells_ub)
-        cap = S.cells_ub;
-    else {
-        const int64_t conc = device_concurrency(kernel);
-        if (conc > 0 && cap > conc)
-            cap -= cap % conc;
+    const size_t cell = sizeof(double) * (size_t(row_planes) * S.ge + size_t(S.col_planes) * S.cg);
+    auto slots = [&](double *p, size_t bytes, int64_t conc) {
+        Slots s;
+        s.cap = int64_t(bytes / cell);
+        if (s.cap >= S.cells_ub)
+            s.cap = S.cells_ub;
+        else if (conc > 0 && s.cap > conc)
+            s.cap -= s.cap % conc;
+        s.row = p;
+        s.col = p + s.cap * row_planes * S.ge;  // symmetric sweep: column slots after the row slots
+        return s;
+    };
+    S.last = slots(S.slots, S.slot_avail, 0);
+    if (S.last.cap == S.cells_ub) {
+        S.early = S.last;
+        S.passes = 1;
+        S.last_cell0 = 0;
+        return;
     }
-    S.cap = cap;
-    S.passes = ceil_div(S.cells_ub, cap);
-    S.scol = S.srow + cap * row_planes * S.ge;  // symmetric sweep: column slots after the row slots
+    const int64_t conc = device_concurrency(kernel);
+    S.last = slots(S.slots, S.slot_avail, conc);
+    S.early = (S.last.cap < conc) ? slots(S.early_slots, S.early_avail, conc) : S.last;
+    const int64_t early = ceil_div(S.cells_ub - S.last.cap, S.early.cap);
+    S.passes = early + 1;
+    S.last_cell0 = (early * S.early.cap < S.cells_ub) ? early * S.early.cap : S.cells_ub - S.last.cap;
 }
 
 // Which of the row and column planes of the slots a fold adds up.
@@ -3273,7 +3304,7 @@ struct FoldSums {
     int rowz[6] = {0}, colz[3] = {0};
 };
 
-FoldArgs fold_args(const Setup &S, const FoldSums &z, int64_t cell0, int64_t ncells, bool first)
+FoldArgs fold_args(const Setup &S, const Slots &slots, const FoldSums &z, int64_t cell0, int64_t ncells, bool first)
 {
     FoldArgs fa = {};
     fa.m = S.cells;
@@ -3294,33 +3325,37 @@ FoldArgs fold_args(const Setup &S, const FoldSums &z, int64_t cell0, int64_t nce
     fa.col_step = int64_t(S.col_planes) * S.cg;
     fa.rows = S.rows;
     fa.rows_pad = S.P.rows_pad;
-    fa.srow = S.srow;
-    fa.scol = S.scol;
+    fa.srow = slots.row;
+    fa.scol = slots.col;
     fa.acc_row = S.acc_row;
     fa.acc_col = S.acc_col;
     return fa;
 }
 
-// Runs the sweep pass by pass: launches the pair kernel over a pass's cells
-// (launch(cell0, grid)) and folds its slots (the sums `all`).  The last pass's fold
-// is left to the caller, which runs it with the finalize: its cells are returned
-// in cell0 and ncells.
-template <typename Launch>
-int sweep_passes(const Setup &S, const Tuning &T, const FoldSums &all, hipStream_t stream, int64_t &cell0,
-                 int64_t &ncells, Launch launch)
+// Runs the sweep pass by pass: launches the pair kernel (launch(args, grid), args with the
+// pass's cells and slots) and folds its slots (the sums `all`).  The last pass's fold
+// is left to the caller, which runs it with the finalize (last_fold).
+template <typename Args, typename Launch>
+int sweep_passes(const Setup &S, const Tuning &T, const FoldSums &all, hipStream_t stream, Args a, Launch launch)
 {
     int rc;
     if (T.t_start && (rc = record_event(T.t_start, stream)) != HAWKES_OK)
         return rc;
     for (int64_t p = 0; p < S.passes; ++p) {
-        cell0 = p * S.cap;
-        ncells = (S.cells_ub - cell0 < S.cap) ? S.cells_ub - cell0 : S.cap;
-        launch(int(cell0), unsigned(ncells));
+        const bool last = (p + 1 == S.passes);
+        const Slots &slots = last ? S.last : S.early;
+        const int64_t cell0 = last ? S.last_cell0 : p * S.early.cap;
+        const int64_t end = last ? S.cells_ub : (p + 2 == S.passes ? S.last_cell0 : cell0 + S.early.cap);
+        a.cells.cell0 = int(cell0);
+        a.cells.ncells = int(end - cell0);
+        a.srow = slots.row;
+        a.scol = slots.col;
+        launch(a, dim3(unsigned(end - cell0)));
         if ((rc = check_launch("pair sweep")) != HAWKES_OK)
             return rc;
-        if (p + 1 == S.passes)
+        if (last)
             break;
-        const FoldArgs fa = fold_args(S, all, cell0, ncells, p == 0);
+        const FoldArgs fa = fold_args(S, slots, all, cell0, end - cell0, p == 0);
         hipLaunchKernelGGL((k_fold<false, false>), dim3(unsigned(ceil_div(S.rows, FOLD_ROWS))),
                            dim3(FOLD_ROWS, unsigned(fa.nrow + fa.ncol)), 0, stream, fa, Fin{});
         if ((rc = check_launch("fold")) != HAWKES_OK)
@@ -3329,7 +3364,13 @@ int sweep_passes(const Setup &S, const Tuning &T, const FoldSums &all, hipStream
     return HAWKES_OK;
 }
 
-// The sweep's cell and slot fields shared by the pair kernels.
+// The fold of the last pass.
+FoldArgs last_fold(const Setup &S, const FoldSums &z)
+{
+    return fold_args(S, S.last, z, S.last_cell0, S.cells_ub - S.last_cell0, S.passes == 1);
+}
+
+// The sweep's cell fields shared by the pair kernels.
 template <typename A>
 void fill_grid(A &a, const Setup &S, const Layout &L)
 {
@@ -3337,8 +3378,6 @@ void fill_grid(A &a, const Setup &S, const Layout &L)
     a.kstrict = S.kstrict;
     a.kend = S.kend;
     a.cells = S.cells;
-    a.srow = S.srow;
-    a.scol = S.scol;
     a.ge = S.ge;
     a.row_begin = int(S.rb);
     a.row_end = int(S.re);
@@ -3465,7 +3504,6 @@ int run(const hawkes_events *ev, const hawkes_theta *th, int precision, int64_t 
         sums = FoldSums{6, 3, {0, 1, 2, 3, 4, 5}, {0, 1, 2}};
     else
         sums = FoldSums{2, 1, {0, 1}, {0}};
-    int64_t cell0 = 0, ncells = 0;
 
     if (is_fp32(precision)) {
         const StageF32 sc = stage_scales(th, uniform);
@@ -3493,17 +3531,15 @@ int run(const hawkes_events *ev, const hawkes_theta *th, int precision, int64_t 
         a.w2 = omega * LOG2E / sc.st;
         a.out_exp = 1.0 / (1.0 + EXP2_MEAN_REL_ERR);
         a.trig_cull = skip.on ? 1 : 0;
-        rc = sweep_passes(S, T, sums, stream, cell0, ncells, [&](int c0, unsigned grid) {
-            a.cells.cell0 = c0;
-            a.cells.ncells = int(grid);
+        rc = sweep_passes(S, T, sums, stream, a, [&](const PairF32 &p, dim3 grid) {
             if (grad && uniform)
-                hipLaunchKernelGGL((k_pair_f32<true, true>), dim3(grid), dim3(WG), 0, stream, a);
+                hipLaunchKernelGGL((k_pair_f32<true, true>), grid, dim3(WG), 0, stream, p);
             else if (grad)
-                hipLaunchKernelGGL((k_pair_f32<true, false>), dim3(grid), dim3(WG), 0, stream, a);
+                hipLaunchKernelGGL((k_pair_f32<true, false>), grid, dim3(WG), 0, stream, p);
             else if (uniform)
-                hipLaunchKernelGGL((k_pair_f32<false, true>), dim3(grid), dim3(WG), 0, stream, a);
+                hipLaunchKernelGGL((k_pair_f32<false, true>), grid, dim3(WG), 0, stream, p);
             else
-                hipLaunchKernelGGL((k_pair_f32<false, false>), dim3(grid), dim3(WG), 0, stream, a);
+                hipLaunchKernelGGL((k_pair_f32<false, false>), grid, dim3(WG), 0, stream, p);
         });
     } else {
         const void *kfn = grad ? reinterpret_cast<const void *>(&k_pair_f64<true>)
@@ -3523,20 +3559,17 @@ int run(const hawkes_events *ev, const hawkes_theta *th, int precision, int64_t 
         a.qh = LOG2E / (2.0 * h0 * h0);
         a.out_g1 = 2.0 * h0 * h0 / LOG2E;
         a.omega = omega * LOG2E;
-        rc = sweep_passes(S, T, sums, stream, cell0, ncells, [&](int c0, unsigned grid) {
-            a.cells.cell0 = c0;
-            a.cells.ncells = int(grid);
+        rc = sweep_passes(S, T, sums, stream, a, [&](const PairF64 &p, dim3 grid) {
             if (grad)
-                hipLaunchKernelGGL(k_pair_f64<true>, dim3(grid), dim3(WG), 0, stream, a);
+                hipLaunchKernelGGL(k_pair_f64<true>, grid, dim3(WG), 0, stream, p);
             else
-                hipLaunchKernelGGL(k_pair_f64<false>, dim3(grid), dim3(WG), 0, stream, a);
+                hipLaunchKernelGGL(k_pair_f64<false>, grid, dim3(WG), 0, stream, p);
         });
     }
     if (rc != HAWKES_OK)
         return rc;
     const Fin f = make_fin(ev, th, precision, S, L, ws, d_lam, d_comp);
-    return finish(f, fold_args(S, sums, cell0, ncells, S.passes == 1), precision, mode, d_loglik, d_grad,
-                  T.t_stop, stream);
+    return finish(f, last_fold(S, sums), precision, mode, d_loglik, d_grad, T.t_stop, stream);
 }
 
 // Several parameter vectors on the same events and rows.  FP32: pairs of
@@ -3606,15 +3639,11 @@ int run_batch(const hawkes_events *ev, const hawkes_theta *th, int64_t num_theta
             a.w2[z] = tz->omega * LOG2E / sc0.st;
         }
         a.trig_cull = skip.on ? 1 : 0;
-        int64_t cell0 = 0, ncells = 0;
-        rc = sweep_passes(S, T, sums, stream, cell0, ncells, [&](int c0, unsigned grid) {
-            a.cells.cell0 = c0;
-            a.cells.ncells = int(grid);
+        rc = sweep_passes(S, T, sums, stream, a, [&](const PairBatchF32 &p, dim3 grid) {
             if (S.uniform)
-                hipLaunchKernelGGL((k_pair_f32_batch<MAX_FUSED_THETA, true>), dim3(grid), dim3(WG), 0, stream, a);
+                hipLaunchKernelGGL((k_pair_f32_batch<MAX_FUSED_THETA, true>), grid, dim3(WG), 0, stream, p);
             else
-                hipLaunchKernelGGL((k_pair_f32_batch<MAX_FUSED_THETA, false>), dim3(grid), dim3(WG), 0, stream,
-                                   a);
+                hipLaunchKernelGGL((k_pair_f32_batch<MAX_FUSED_THETA, false>), grid, dim3(WG), 0, stream, p);
         });
         if (rc != HAWKES_OK)
             return rc;
@@ -3624,9 +3653,8 @@ int run_batch(const hawkes_events *ev, const hawkes_theta *th, int64_t num_theta
             Fin f = make_fin(ev, t0 + z, precision, S, L, ws, nullptr, nullptr);
             f.rescue_count += z;
             f.ticket += z;
-            if ((rc = finish(f, fold_args(S, own, cell0, ncells, S.passes == 1), precision, MODE_LOGLIK,
-                             d_loglik + k + z, nullptr, z + 1 == MAX_FUSED_THETA ? T.t_stop : nullptr, stream)) !=
-                HAWKES_OK)
+            if ((rc = finish(f, last_fold(S, own), precision, MODE_LOGLIK, d_loglik + k + z, nullptr,
+                             z + 1 == MAX_FUSED_THETA ? T.t_stop : nullptr, stream)) != HAWKES_OK)
                 return rc;
         }
     }
