@@ -132,13 +132,19 @@ def precision_code(precision) -> int:
         raise ValueError(f"unknown precision {precision!r}") from None
 
 
+# torch's current stream of a device as the bare handle; not a public function, so not every torch need have it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def stream_handle(stream: torch.cuda.Stream | None = None) -> int:
     """The hipStream_t of `stream`, else of the current device's current stream.  The latter is asked for as
-    the bare handle: a torch.cuda.Stream object built only to be read costs several microseconds, as
-    long as the launch it precedes."""
+    the bare handle where torch gives it: a torch.cuda.Stream object built only to be read costs several
+    microseconds, as long as the launch it precedes."""
     if stream is not None:
         return int(stream.cuda_stream)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return int(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
 
 
 def theta_struct(theta) -> Theta:
