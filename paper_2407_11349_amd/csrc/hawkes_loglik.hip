@@ -791,7 +791,8 @@ __device__ inline void geom_da_uni(double xn, double yn, double tn, double xm, d
 // source sits 8 lanes away from the second half's (row_ror:8) and the halves
 // meet in FP64.  The four rows take the same sources at the same lane
 // positions and are added by the gfx950 row swaps (below).
-constexpr int DPP_ROW_ROR8 = 0x128, DPP_ROW_ROR15 = 0x12F;
+constexpr int DPP_ROW_ROR1 = 0x121, DPP_ROW_ROR2 = 0x122, DPP_ROW_ROR4 = 0x124, DPP_ROW_ROR8 = 0x128,
+              DPP_ROW_ROR15 = 0x12F;
 template <int CTRL>
 __device__ __forceinline__ int dpp_mov(int v)
 {
@@ -2242,12 +2243,14 @@ __device__ __forceinline__ double exp2_nonpos(double y, const double *table)
     return ldexp(fma(e[0], q, e[0]), n >> 4);
 }
 
-__device__ __forceinline__ double row_rotate_f64(double v)
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov_f64(double v)
 {
     const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-    const int lo = dpp_mov<DPP_ROW_ROR15>(int(unsigned(u))), hi = dpp_mov<DPP_ROW_ROR15>(int(unsigned(u >> 32)));
+    const int lo = dpp_mov<CTRL>(int(unsigned(u))), hi = dpp_mov<CTRL>(int(unsigned(u >> 32)));
     return make_f64(unsigned(lo), unsigned(hi));
 }
+__device__ __forceinline__ double row_rotate_f64(double v) { return dpp_mov_f64<DPP_ROW_ROR15>(v); }
 
 // The FP64 sweep: every pair term in FP64 with the direct formulas, on the
 // same work decomposition as the FP32 sweep (row groups x column groups; over
@@ -2747,22 +2750,55 @@ __global__ __launch_bounds__(FOLD_ROWS * 9) void k_fold(FoldArgs a, Fin f)
         f.comp_out[r] = bad ? __builtin_nan("") : comp;
 }
 
-// FP64 rescue: rows whose FP32 rate is underflow-limited are swept again
-// with every pair in FP64 (one workgroup of WGS threads per row, lanes strided over
-// sources), and their row values are replaced.  Workgroups stride over the
-// rescue list, so the grid size is independent of its length.
-template <bool GRAD, int WGS>
-__device__ void rescue_rows(const Fin &f, int count)
+constexpr int REDUCE_WG = 1024;
+constexpr int REDUCE_WAVES = REDUCE_WG / 64;
+
+// The sum over each row of 16 lanes, in every lane
+__device__ __forceinline__ double row_sum_f64(double v)
 {
-    __shared__ double red[6][WGS];
-    const int tid = threadIdx.x;
-    for (int w = blockIdx.x; w < count; w += gridDim.x) {
-        const int64_t r = f.rescue[w];
+    v += dpp_mov_f64<DPP_ROW_ROR8>(v);
+    v += dpp_mov_f64<DPP_ROW_ROR4>(v);
+    v += dpp_mov_f64<DPP_ROW_ROR2>(v);
+    v += dpp_mov_f64<DPP_ROW_ROR1>(v);
+    return v;
+}
+
+// FP64 rescue: rows whose FP32 rate is underflow-limited are swept again
+// with every pair in FP64 (lanes strided over sources), and their row values
+// are replaced.  Workgroups stride over the rescue list, so the grid size is
+// independent of its length.  A row is taken by a team of 1 to 16 waves, whichever gets through the list
+// in the fewest steps of 64 sources per wave, two of them (a sum over lanes, the row's terms, with more than one wave
+// two barriers) counted for each round of rows: of a small set many rows are in flight, a wave each; a
+// single row of a large one takes a whole workgroup.  Calls (value only, FP32) with teams of 4 waves, of 16,
+// and so: every row of 100 events 291, 446, 63 us, of 700 729, 1083, 124, of 2,000 932, 1238, 169;
+// one row in twenty of 20,000 732, 420, 405.
+//   True in the threads that have written a row.
+template <bool GRAD>
+__device__ bool rescue_rows(const Fin &f, int count)
+{
+    bool wrote = false;
+    __shared__ double part[6][REDUCE_WAVES];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int team = 1;  // waves per row
+    uint64_t least = UINT64_MAX;
+#pragma unroll
+    for (int k = 0; 1 << k <= REDUCE_WAVES; ++k) {
+        const unsigned at_once = gridDim.x * (REDUCE_WAVES >> k);
+        const uint64_t steps = uint64_t((unsigned(count) + at_once - 1) / at_once) * (((f.n + (64 << k) - 1) >> (6 + k)) + 2);
+        if (steps < least) {
+            least = steps;
+            team = 1 << k;
+        }
+    }
+    const int rows = REDUCE_WAVES / team, own = wave / team, sub = wave % team;
+    for (int w0 = blockIdx.x * rows; w0 < count; w0 += gridDim.x * rows) {
+        const bool in = w0 + own < count;
+        const int64_t r = f.rescue[in ? w0 + own : w0];
         const int64_t i = f.row_begin + r;
         const double xn = f.x[i], yn = f.y[i], tn = f.t[i];
         const int gn = f.g[i];
         double S[6] = {0, 0, 0, 0, 0, 0};
-        for (int64_t m = tid; m < f.n; m += WGS) {
+        for (int64_t m = 64 * sub + lane; m < f.n; m += 64 * team) {
             const int gm = f.g[m];
             if (gm == gn)
                 continue;
@@ -2782,28 +2818,32 @@ __device__ void rescue_rows(const Fin &f, int count)
                 S[5] += e * dt;
             }
         }
+#pragma unroll
         for (int z = 0; z < 6; ++z)
-            red[z][tid] = S[z];
-        __syncthreads();
-        for (int h = WGS / 2; h > 0; h >>= 1) {
-            if (tid < h)
+            S[z] = sum_rows_f64(row_sum_f64(S[z]));
+        if (team > 1) {  // a lane per wave of the team
+            if (lane == 0)
+#pragma unroll
                 for (int z = 0; z < 6; ++z)
-                    red[z][tid] += red[z][tid + h];
+                    part[z][wave] = S[z];
+            __syncthreads();
+#pragma unroll
+            for (int z = 0; z < 6; ++z)
+                S[z] = row_sum_f64((lane & 15) < team ? part[z][own * team + (lane & 15)] : 0.0);
             __syncthreads();
         }
-        if (tid == 0) {
-            double T6[6], v[7] = {0, 0, 0, 0, 0, 0, 0}, lam, comp;
-            for (int z = 0; z < 6; ++z)
-                T6[z] = red[z][0];
-            row_terms<GRAD>(f, T6, tn, f.t[f.n - 1], v, lam, comp);
+        if (in && sub == 0 && lane == 0) {
+            double v[7] = {0, 0, 0, 0, 0, 0, 0}, lam, comp;
+            row_terms<GRAD>(f, S, tn, f.t[f.n - 1], v, lam, comp);
             const int nv = GRAD ? 7 : 1;
             for (int z = 0; z < nv; ++z)
                 f.rowvals[r * ROW_VALUES + z] = v[z];
             if (f.lam_out && f.status[0] == 0)
                 f.lam_out[r] = lam;
+            wrote = true;
         }
-        __syncthreads();
     }
+    return wrote;
 }
 
 // Rescue and the sums of all rows, in one launch: with no row to rescue (as a rule) the
@@ -2814,25 +2854,25 @@ __device__ void rescue_rows(const Fin &f, int count)
 // one of 20,000 144.0 instead of 141.6.  A row's values lie together, so that the first
 // workgroup's strided reads touch one line per group (by planes it took 25 us at 1e5 rows,
 // now 9).
-constexpr int REDUCE_WG = 1024;
 template <bool GRAD>
 __global__ __launch_bounds__(REDUCE_WG) void k_finish_rows(Fin f, int sums, double *loglik, double *grad)
 {
     constexpr int nv = GRAD ? 7 : 1;
-    __shared__ double red[nv][REDUCE_WG / 64];
+    __shared__ double red[nv][REDUCE_WAVES];
     __shared__ int last;
     const int tid = threadIdx.x, count = *f.rescue_count, bad = f.status[0];
     if (count == 0) {
         if (blockIdx.x != 0 || !sums)
             return;
     } else {
-        rescue_rows<GRAD, REDUCE_WG>(f, count);
+        const bool wrote = rescue_rows<GRAD>(f, count);
         if (!sums)
             return;
-        if (tid == 0) {
-            __threadfence();  // this workgroup's rows before its ticket
+        if (wrote)
+            __threadfence();  // the thread's rows before the workgroup's ticket
+        __syncthreads();
+        if (tid == 0)
             last = atomicAdd(f.ticket, 1) == int(gridDim.x) - 1;
-        }
         __syncthreads();
         if (!last)
             return;
@@ -2867,7 +2907,7 @@ __global__ __launch_bounds__(REDUCE_WG) void k_finish_rows(Fin f, int sums, doub
     if (tid < nv) {
         double s = 0.0;
 #pragma unroll
-        for (int w = 0; w < REDUCE_WG / 64; ++w)
+        for (int w = 0; w < REDUCE_WAVES; ++w)
             s += red[tid][w];
         const double out = bad ? __builtin_nan("") : s;
         if (tid == 0) {
