@@ -2473,7 +2473,7 @@ __global__ __launch_bounds__(WG) HK_WAVES(GRAD ? 3 : 4) void k_pair_f64(PairF64 
                 } else if (cls == ANTI) {
                     for (int m = mlo; m < mend; ++m)
                         pair(load(tbase + m * 8), 0, Anti{}, c0, c1, c2);
-                } else {
+                } else if (!(first == last && t_lo == t_hi && first == t_lo)) {  // one time for all: no terms
                     for (int m = mlo; m < mend; ++m)
                         pair(load(tbase + m * 8), lg[m], Masked{}, c0, c1, c2);
                 }
