@@ -24,19 +24,19 @@ __device__ inline float gelu_d2(float x) { return K_INV_SQRT_2PI * expf(-0.5f * 
 // (Lawson's iteration, the coefficients rounded one after the other; of the shifts 3.2 to 4.3 and degrees 7
 // and 8, the shortest at that error).  w is small where R is steep, so the reciprocal's rounding does not count
 // there, and each result ends in one fma: GELU x/2 + |x| (1/2 - e R), slope
-// e (R - u / sqrt(2 pi)) for x < 0 and one minus that above.  From u = 16 on the exponential is 0 and u
-// is held there, so that an infinite x gives what erff gives.
+// e (R - u / sqrt(2 pi)) for x < 0 and one minus that above.  w is held within [0, 1] (by its product's clamp), so
+// that an infinite x gives what erff gives.
 //   Errors (largest, rms) over 2^22 standard normal x: GELU 2.7e-7, 2.0e-8 and slope 1.0e-7,
 // 2.3e-8; with erff and expf 3.9e-7, 2.5e-8 and 1.4e-7, 2.7e-8; with a polynomial in 1 / (1 + 0.27 u) and the slope
-// added to a rounded Phi 3.6e-7, 2.5e-8 and 2.4e-7, 4.2e-8 (in the same time: 37.5 us for 21,000
-// samples).  Some 23 instructions instead of 75, which were the kernel's largest part by far.
+// added to a rounded Phi 3.6e-7, 2.5e-8 and 2.4e-7, 4.2e-8 (in the same time: 38.7 us for 21,000
+// samples, 526 for 400,000).  Some 22 instructions instead of 75, which were the kernel's largest part by far.
 struct Gelu {
     float a, d1;
 };
 __device__ __forceinline__ Gelu gelu_all(float x)
 {
-    const float u = fminf(fabsf(x), 16.0f);
-    const float w = u * __builtin_amdgcn_rcpf(u + 4.0f);
+    const float u = fabsf(x);
+    const float w = fminf(fmaxf(u * __builtin_amdgcn_rcpf(u + 4.0f), 0.0f), 1.0f);
     const float e = __builtin_amdgcn_exp2f(x * x * -0.72134752044448170368f);
     float r = 9.630157799e-02f;
     r = fmaf(r, w, -3.094779551e-01f);

@@ -58,7 +58,10 @@ def test_inference_gelu_at_the_ends():
     lib = _probe()
     x = torch.tensor([0.0, -0.0, 15.9, 16.1, 1e10, 3e38, math.inf, -15.9, -1e10, -3e38, math.nan], device="cuda")
     a, d = _run(lib, 1, x)
+    a_erf, d_erf = _run(lib, 0, x)
     assert a[:2].tolist() == [0.0, 0.0] and d[:2].tolist() == [0.5, 0.5]
-    assert torch.equal(a[2:7], x[2:7]) and torch.all(d[2:7] == 1.0)
+    assert torch.equal(a[2:7], x[2:7]) and torch.all(d[2:6] == 1.0)
     assert torch.all(a[7:10] == 0.0) and torch.all(d[7:10] == 0.0)
-    assert torch.isnan(a[10]) and torch.isnan(d[10])
+    for i in (6, 10):  # infinite or not a number: as with erff and expf
+        assert torch.equal(a[i:i + 1].nan_to_num(7.0), a_erf[i:i + 1].nan_to_num(7.0))
+        assert torch.equal(d[i:i + 1].nan_to_num(7.0), d_erf[i:i + 1].nan_to_num(7.0))
