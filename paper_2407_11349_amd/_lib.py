@@ -36,7 +36,7 @@ EXPORTS = (
 )
 # hawkes_mlp_leapfrog_io: 42 doubles (z, p, grad, inv_mass, m_z, s_z: 6 each; m_y, s_y, prior_var, eps, s, status)
 LEAPFROG_IO_DOUBLES = 42
-# hawkes_options.symmetric_groups: blocks up to which the default plan has one per group, largest accepted count
+# hawkes_options.symmetric_groups: blocks up to which the default plan picks its cells' width, largest accepted count
 SYM_GROUPS_DEFAULT = 384
 SYM_GROUPS_MAX = 1024
 ROW_WGS_MAX = 65536

@@ -104,8 +104,9 @@ constexpr int GS = HAWKES_GS;             // FP32 terms summed before folding in
 // row sweep: workgroups (target blocks x source chunks) a call aims for
 constexpr int64_t DEFAULT_ROW_WGS = 32768;
 constexpr int64_t MAX_ROW_WGS = 65536;
-// Row groups of the symmetric sweep: one target block each up to
-// DEFAULT_SYM_GROUPS blocks, above that at most PLAN_GROUPS groups of several.  A pass
+// Row groups of the symmetric sweep: one target block each up to PLAN_GROUPS
+// blocks, above that at most PLAN_GROUPS groups of several.  (DEFAULT_SYM_GROUPS: the blocks up to which the
+// default plan picks the width of column groups, and the groups whose cell the smallest workspace holds.)  A pass
 // ends when its last workgroup does, and the chip idles for about a third of a
 // cell's time: smaller cells (3 blocks x 6 tiles at 10^6 events) lose less there and
 // write more partial sums.  At 10^6 events in the default workspace, full sweep /
@@ -193,18 +194,23 @@ SymPlan make_sym_plan(int64_t n, int groups)
     return finish_sym_plan(n, rr, rr * TB);
 }
 
-// The default plan.  Above 384 blocks row groups hold several.  Below, a row
+// The default plan.  Above 384 blocks row groups and column groups hold as many events, one block up to 652
+// blocks and several from there.  Below, a row
 // group is one block, and what counts is how its cells fill the chip: a cell of
 // 512 sources is 512 dependent steps of its waves, and few of them leave most
-// of the chip idle (at 2,000 events 16 cells took 93 us, 162 of 32 sources take
+// of the chip idle (at 2,000 events 16 cells took 93 us, 160 of 32 sources take
 // 13).  Up to one cell per CU, as narrow as gives that many (a wider cell is
 // longer, more cells than CUs are packed three to a CU while others idle); at most
 // 256 sources, since from there on several rounds of narrower ones are shorter.
 // Measured calls (FP32 gradient, us) for widths 32 / 64 / 128 / 256 / 512: 2,000
 // events 34 / 36 / 47 / 63 / 98, 5,000 events 57 / 54 / 48 / 63 / 98, 7,000 events
-// 74 / 65 / 70 / 65 / 99, 10,000 events 139 / 101 / 86 / 107 / 101, 20,000 events
-// - / 275 / 205 / 204 / 239 (skip mode - / - / 150 / 159 / 196), 45,000 events
-// - / - / 897 / 762 / 780.
+// 74 / 65 / 70 / 65 / 99.  Beside the lines at 40 and 96 blocks, for 64 / 128 / 256 / 512 (skip mode, waves):
+//   16,000 events  156 / 145 / 151 / 183  (120 / 115 / 115 / 184)
+//   20,480 events  227 / 199 / 200 / 229  (161 / 152 / 156 / 204)
+//   26,000 events  361 / 300 / 293 / 318  (222 / 198 / 200 / 212)
+//   45,000 events  1080 / 872 / 754 / 767  (612 / 479 / 438 / 461)
+//   49,152 events  1278 / 1023 / 901 / 900  (716 / 560 / 507 / 523)
+//   60,000 events  1955 / 1538 / 1364 / 1319  (1047 / 833 / 726 / 727)
 SymPlan default_sym_plan(int64_t n)
 {
     const int64_t tb = ceil_div(n, TB);
@@ -2208,7 +2214,7 @@ struct PairF64 {
 // formed in units of log2): y = n/16 + r with n = rint(16 y) and |r| <= 1/32,
 // 2^y = 2^(n >> 4) T_j (1 + d_j + r P(r)), j = n & 15, where T_j is 2^(j/16) rounded to
 // FP64 and d_j what that rounding left out (relative), so that only the last
-// fma and the scaling round at full size (0.51 ulp).  P is the degree-5
+// fma and the scaling round at full size (0.66 ulp at worst, just below a power of two).  P is the degree-5
 // interpolant of (2^r - 1)/r at the Chebyshev nodes of [-1/32, 1/32] (error of
 // 2^r below 1.5e-17 relative).  n comes from the low word of 16 y + 1.5 2^52.
 // 11 FP64 operations where a degree-12 polynomial over |r| <= 1/2 took 17.  The 16
@@ -3749,8 +3755,8 @@ extern "C" size_t hawkes_workspace_bytes(int64_t n, int precision)
 // pointer (that would be a host-side stand-in, not a device address): the
 // device address is looked up once per device with hipGetSymbolAddress and
 // kept.  Calls on one GPU share the array, so calls that overlap on one GPU
-// race; every call clears what must start at zero (status word,
-// accumulators) and stages the rest afresh.
+// race; every call writes what it reads afresh (status words and plan, staged
+// records, and the accumulators in the first fold).
 
 constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(64) << 20;
 constexpr int NOALLOC_MAX_DEVICES = 64;

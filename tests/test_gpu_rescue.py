@@ -44,7 +44,7 @@ def test_rescued_rows_by_list_length(n, alone):
 
 @pytest.mark.parametrize("n", [100, 700, 2000])
 def test_time_with_every_row_rescued(n):
-    """At most 8 times a call without any (13 and more with a workgroup of 16 waves for every row)."""
+    """At most 12 times a call without any (20 to 50 times with a workgroup of 16 waves for every row)."""
     ev = synth.generate(synth.N2K, n=n, seed=5)
     th, ms = synth.theta_default(), []
     for t in (ev.t, np.full(n, 3.0)):  # all times tied: no rate at all, every row is recomputed
@@ -60,4 +60,4 @@ def test_time_with_every_row_rescued(n):
             best = min(best, 100.0 * a.elapsed_time(b))
         ms.append(best)
     print(f"n={n}: {ms[0]:.1f} us, every row rescued {ms[1]:.1f} us", flush=True)
-    assert ms[1] < 8.0 * ms[0]
+    assert ms[1] < 12.0 * ms[0]
